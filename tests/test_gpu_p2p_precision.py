@@ -1,5 +1,6 @@
 """How exact one pair of the near field is, against FP64: the reciprocal of
-the squared distance (field, and the charge's and position's gradients)."""
+the squared distance (field, and the charge's and position's gradients), and
+the angle (Im phi, and the charge's gradient of a loss on it)."""
 import numpy as np
 import pytest
 
@@ -67,3 +68,71 @@ def test_gradients_have_the_reciprocals_precision(c):
     B.p2p_backward(pts, q, lsn, one, ls1, 2, cphi, None, gq, G)
     ref = -c / (-d.astype(np.float64) @ [1, 1j])
     assert _rms(G.cpu().numpy().astype(np.complex128), ref) < RMS
+
+
+def _angles(offsets):
+    """(Im phi of a unit source at (1/8, 1/8) at the points around it, its exact
+    value for the FP32 differences; the same with the points as sources and the
+    charge's gradient of Im phi)."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    centre = np.full((1, 2), 0.125, np.float32)
+    t = (centre + offsets).astype(np.float32)
+    n = len(t)
+    perm, lsn = B.build_tree(torch.from_numpy(t).cuda(), 2)
+    assert np.array_equal(perm.cpu().numpy(), np.arange(n))  # one leaf
+    pts, one = torch.from_numpy(t).cuda(), torch.from_numpy(centre).cuda()
+    ls1 = B.build_tree(one, 2)[1]
+    phi, _ = B.p2p(one, torch.ones(1, device="cuda"), ls1, pts, lsn, 2)
+    d = (t - centre).astype(np.float64)  # FP32 differences, as the kernel's
+    gq, G = torch.zeros(n, device="cuda"), torch.zeros(n, dtype=torch.complex64, device="cuda")
+    c = torch.full((1,), -1j, dtype=torch.complex64, device="cuda")  # Re(c log r) = arg r
+    B.p2p_backward(pts, torch.ones(n, device="cuda"), lsn, one, ls1, 2, c, None, gq, G)
+    return ((phi.imag.cpu().numpy().astype(np.float64), np.arctan2(d[:, 1], d[:, 0])),
+            (gq.cpu().numpy().astype(np.float64), np.arctan2(-d[:, 1], -d[:, 0])))
+
+
+def test_angle_of_all_directions_is_no_worse_than_an_arctangents():
+    """0.67e-7 rms over all directions; the arc tangent of the legs' ratio, with
+    one reciprocal good to 1 ulp and the quadrant's angles subtracted after it,
+    has 0.79e-7, the arc sine from the diagonal alone 0.85e-7."""
+    g = np.random.Generator(np.random.PCG64(6))
+    th, rad = 2 * np.pi * g.random(200000), np.exp2(-9.0 + 5.9 * g.random(200000))
+    for got, ref in _angles(rad[:, None] * np.stack([np.cos(th), np.sin(th)], 1)):
+        assert np.sqrt(np.mean((got - ref) ** 2)) < 7.3e-8
+
+
+def test_small_angles_are_relatively_exact():
+    """Relative bound: the reciprocal root's 1.2e-7, half of r^2's two roundings
+    of 0.6e-7, and one rounding each of the product, the polynomial's last step
+    and the sum: 3.6e-7."""
+    g = np.random.Generator(np.random.PCG64(7))
+    small = np.exp2(-17.0 + 10.0 * g.random(20000)) * np.where(g.random(20000) < 0.5, -1, 1)
+    right, left = (np.stack([s * np.full(20000, 0.0625), 0.0625 * small], 1) for s in (1, -1))
+    (got, ref), _ = _angles(right)
+    assert np.all(np.abs(got - ref) <= 3.7e-7 * np.abs(ref))
+    _, (got, ref) = _angles(left)  # towards the centre from its left: angles near 0
+    assert np.all(np.abs(got - ref) <= 3.7e-7 * np.abs(ref))
+
+
+def test_angle_on_the_axes_is_exact():
+    k = np.arange(1, 60) / 512.0
+    z = np.zeros_like(k)
+    pi, half = np.float32(np.pi), np.float32(np.pi / 2)
+    for off, want, back in ((np.stack([k, z], 1), 0.0, pi), (np.stack([-k, z], 1), pi, 0.0),
+                            (np.stack([z, k], 1), half, -half), (np.stack([z, -k], 1), -half, half)):
+        (got, _), (gq, _) = _angles(off)
+        assert np.all(got == want) and np.all(gq == back)
+
+
+def test_charges_in_a_row_add_no_angle():
+    """Equal charges to the left of a target on its own horizontal line: Im phi
+    is a sum of zeros, however many they are."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    x = np.linspace(0.26, 0.7, 5000).astype(np.float32)
+    src = torch.from_numpy(np.stack([x, np.full_like(x, 0.3)], 1)).cuda()
+    t = torch.tensor([[0.74, 0.3]], dtype=torch.float32, device="cuda")
+    perm, ls = B.build_tree(src, 2)
+    phi, _ = B.p2p(B.gather(src, perm), torch.ones(len(x), device="cuda"), ls, t, B.build_tree(t, 2)[1], 2)
+    assert phi.imag.item() == 0.0
