@@ -136,3 +136,33 @@ def test_charges_in_a_row_add_no_angle():
     perm, ls = B.build_tree(src, 2)
     phi, _ = B.p2p(B.gather(src, perm), torch.ones(len(x), device="cuda"), ls, t, B.build_tree(t, 2)[1], 2)
     assert phi.imag.item() == 0.0
+
+
+def test_rows_outside_the_square_see_their_columns_alone():
+    """The near field takes rows wherever they are: a target (and, in the
+    transpose, a source) at (4, 4) filed under a leaf of crowded neighbours
+    interacts with the columns there and nothing else.  Tolerance as in the
+    other near-field tests, 1e-5 of the largest value."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    g = np.random.Generator(np.random.PCG64(8))
+    cols = ((np.array([1, 2]) + g.random((41, 2))) / 4).astype(np.float32)  # one other leaf, not whole phases
+    rows = np.array([[4, 4], [4, 4], [0.3, 0.3]], np.float32)
+    leaf, own = 9, 3  # Morton indices of (1, 2) and (1, 1)
+    ls = np.where(np.arange(17) <= leaf, 0, len(cols)).astype(np.int32)
+    rls = np.where(np.arange(17) <= own, 0, len(rows)).astype(np.int32)
+    C, R, L, RL = (torch.from_numpy(a).cuda() for a in (cols, rows, ls, rls))
+    qc = g.random(len(cols)).astype(np.float32)
+    phi, f = B.p2p(C, torch.from_numpy(qc).cuda(), L, R, RL, 2)
+    r = rows.astype(np.float64) @ [1, 1j]
+    r = r[:, None] - (cols.astype(np.float64) @ [1, 1j])[None, :]
+    pr, fr = np.log(r) @ qc.astype(np.float64), (1 / r) @ qc.astype(np.float64)
+    assert np.abs(phi.cpu().numpy() - pr).max() < 1e-5 * np.abs(pr).max()
+    assert np.abs(f.cpu().numpy() - fr).max() < 1e-5 * np.abs(fr).max()
+    cphi = (g.standard_normal(len(cols)) + 1j * g.standard_normal(len(cols))).astype(np.complex64)
+    for c in (cphi, cphi.real.astype(np.complex64)):
+        gq, G = torch.zeros(3, device="cuda"), torch.zeros(3, dtype=torch.complex64, device="cuda")
+        B.p2p_backward(R, torch.ones(3, device="cuda"), RL, C, L, 2, torch.from_numpy(c).cuda(), None, gq, G)
+        gqr, Gr = (np.log(-r) @ c.astype(np.complex128)).real, (1 / r) @ c.astype(np.complex128)
+        assert np.abs(gq.cpu().numpy() - gqr).max() < 1e-5 * np.abs(gqr).max()
+        assert np.abs(G.cpu().numpy() - Gr).max() < 1e-5 * np.abs(Gr).max()
