@@ -1,0 +1,58 @@
+"""The largest point sets the entry points take, 2^31 - 1 points: index
+arithmetic at the end of the range.  Only the points that a test's results
+depend on are written; the arrays are left as allocated otherwise (nothing
+that is checked reads them)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+N = 2 ** 31 - 1
+
+
+def _last_leaves(counts):
+    """Points of the leaves (6, 6), (7, 6), (6, 7), (7, 7) of depth 3, the last
+    ones in Morton order, and the leaf starts of N points that end with them:
+    all others in leaf 0."""
+    g = np.random.Generator(np.random.PCG64(3))
+    corner = [(6, 6), (7, 6), (6, 7), (7, 7)]
+    pts = np.concatenate([(np.array(c) + 0.02 + 0.96 * g.random((k, 2))) / 8 for c, k in zip(corner, counts)])
+    ends = np.full(65, N - sum(counts), np.int64)
+    ends[0] = 0
+    ends[61:65] = N - sum(counts) + np.cumsum(counts)
+    return pts.astype(np.float32), ends.astype(np.int32)
+
+
+def _last_rows(values):
+    """A device array of N rows that ends with the given ones."""
+    import torch
+    v = torch.from_numpy(np.ascontiguousarray(values))
+    a = torch.empty((N,) + tuple(v.shape[1:]), dtype=v.dtype, device="cuda")
+    a[N - len(v):] = v.cuda()
+    return a
+
+
+@pytest.mark.parametrize("counts", [(20, 9, 17, 30), (130, 40, 5, 90)], ids=["staged whole", "lists"])
+def test_near_field_columns_at_the_end_of_the_range(counts):
+    """A few rows in the last leaf, whose columns end with the last of 2^31 - 1.
+    Tolerance as in the other near-field tests."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    print(f"near field, columns end at 2^31 - 1, {counts}", flush=True)
+    cols, ls = _last_leaves(counts)
+    g = np.random.Generator(np.random.PCG64(4))
+    rows = ((np.array([7, 7]) + g.random((5, 2))) / 8).astype(np.float32)
+    rls = np.where(np.arange(65) <= 63, 0, 5).astype(np.int32)
+    q = g.standard_normal(len(cols)).astype(np.float32)
+    X, L, R, RL = _last_rows(cols), torch.from_numpy(ls).cuda(), torch.from_numpy(rows).cuda(), torch.from_numpy(rls).cuda()
+    r = (rows.astype(np.float64) @ [1, 1j])[:, None] - (cols.astype(np.float64) @ [1, 1j])[None, :]
+    phi, f = B.p2p(X, _last_rows(q), L, R, RL, 3)
+    pr, fr = np.log(r) @ q.astype(np.float64), (1 / r) @ q.astype(np.float64)
+    assert np.abs(phi.cpu().numpy() - pr).max() < 1e-5 * np.abs(pr).max()
+    assert np.abs(f.cpu().numpy() - fr).max() < 1e-5 * np.abs(fr).max()
+    c = (g.standard_normal(len(cols)) + 1j * g.standard_normal(len(cols))).astype(np.complex64)
+    gq, G = torch.zeros(5, device="cuda"), torch.zeros(5, dtype=torch.complex64, device="cuda")
+    B.p2p_backward(R, torch.ones(5, device="cuda"), RL, X, L, 3, _last_rows(c), None, gq, G)
+    gqr, Gr = (np.log(-r) @ c.astype(np.complex128)).real, (1 / r) @ c.astype(np.complex128)
+    assert np.abs(gq.cpu().numpy() - gqr).max() < 1e-5 * np.abs(gqr).max()
+    assert np.abs(G.cpu().numpy() - Gr).max() < 1e-5 * np.abs(Gr).max()
