@@ -114,8 +114,8 @@ __global__ __launch_bounds__(256) void p2m_kernel(const float2 *__restrict__ xy,
   float ar[P], ai[P];
 #pragma unroll
   for (int k = 0; k < P; ++k) ar[k] = ai[k] = 0.f;
-  const int32_t e = ls[m + 1];
-  for (int32_t s = ls[m] + r; s < e; s += LANES) {
+  const uint32_t e = ls[m + 1];  // unsigned: the step may pass 2^31
+  for (uint32_t s = uint32_t(ls[m]) + r; s < e; s += LANES) {
     const float2 w = scaled_offset(xy[s], uint32_t(m), depth);
     float pr = q[s], pi = 0.f;  // q w^k
 #pragma unroll
@@ -545,8 +545,8 @@ __global__ __launch_bounds__(256) void l2p_backward_kernel(const float2 *__restr
 #pragma unroll
   for (int n = 0; n < P; ++n) ar[n] = ai[n] = 0.0;
   double sbr = 0.0, sbi = 0.0;
-  const int32_t e = tls[m + 1];
-  for (int32_t t = tls[m] + r; t < e; t += LANES) {
+  const uint32_t e = tls[m + 1];  // unsigned: the step may pass 2^31
+  for (uint32_t t = uint32_t(tls[m]) + r; t < e; t += LANES) {
     const float2 z = txy[t];
     const double wr = (double(z.x) - cx) * ih, wi = (double(z.y) - cy) * ih;
     double cr = 0.0, ci = 0.0, dr = 0.0, di = 0.0;  // cphi w^n, cfield w^n / h

@@ -56,3 +56,38 @@ def test_near_field_columns_at_the_end_of_the_range(counts):
     gqr, Gr = (np.log(-r) @ c.astype(np.complex128)).real, (1 / r) @ c.astype(np.complex128)
     assert np.abs(gq.cpu().numpy() - gqr).max() < 1e-5 * np.abs(gqr).max()
     assert np.abs(G.cpu().numpy() - Gr).max() < 1e-5 * np.abs(Gr).max()
+
+
+DEPTH = 12  # 128 points a leaf, one less in the last
+
+
+def _even_leaves():
+    import torch
+    return (torch.arange(4 ** DEPTH + 1, dtype=torch.int64, device="cuda") * 128).clamp_(max=N).to(torch.int32)
+
+
+def _last_leaf_points():
+    g = np.random.Generator(np.random.PCG64(6))
+    off = g.random((127, 2)) - 0.5  # from the leaf's centre, in leaf widths
+    xy = ((2 ** DEPTH - 0.5 + off) / 2 ** DEPTH).astype(np.float32)
+    return xy, (xy.astype(np.float64) * 2 ** DEPTH - (2 ** DEPTH - 0.5)) @ [1, 1j]
+
+
+def test_leaf_sums_at_the_end_of_the_range():
+    """P2M and L2P^T of the last leaf.  FP32 and FP64 sums of 127 terms of at
+    most 1 against FP64: 1e-5 of the largest coefficient."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    print("leaf sums, points end at 2^31 - 1", flush=True)
+    p = 8
+    xy, w = _last_leaf_points()
+    g = np.random.Generator(np.random.PCG64(7))
+    q, c = g.standard_normal(127).astype(np.float32), g.standard_normal(127).astype(np.complex64)
+    X, L = _last_rows(xy), _even_leaves()
+    M = B.p2m(X, _last_rows(q), L, DEPTH, p)[-1].cpu().numpy()
+    ref = np.array([np.sum(q * w ** k) for k in range(p)])
+    assert np.abs(M - ref).max() < 1e-5 * np.abs(ref).max()
+    gL, gb = B.l2p_backward(X, L, _last_rows(c), None, DEPTH, p)
+    ref = np.array([np.sum(c * w ** (k + 1)) / (k + 1) for k in range(p)])
+    assert np.abs(gL[-1].cpu().numpy() - ref).max() < 1e-5 * np.abs(ref).max()
+    assert abs(gb[-1].item() - c.sum()) < 1e-5 * np.abs(c).sum()
