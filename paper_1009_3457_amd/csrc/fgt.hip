@@ -64,12 +64,12 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
   // rows and columns past P repeat row 0 and are not stored
   const double *w1 = pow12[wave][0] + (row < P ? row : 0) * kPowRow + kq;
   const double *w2 = pow12[wave][1] + (row < P ? row : 0) * kPowRow + kq;
-  const int32_t jb = ls[m], je = ls[m + 1];
+  const uint32_t jb = ls[m], je = ls[m + 1];  // unsigned: a step may pass 2^31
   const float *co = reinterpret_cast<const float *>(xy) + axis;
   float xn = 0.f, qn = 0.f;
   if (jb + src < je) xn = co[2 * int64_t(jb + src)], qn = q[jb + src];
-  for (int32_t j0 = jb; j0 < je; j0 += 32) {
-    const int cnt = min(32, int(je - j0));
+  for (uint32_t j0 = jb; j0 < je; j0 += 32) {
+    const int cnt = int(min(32u, je - j0));
     const bool live = src < cnt;  // a source past the end has charge 0
     const double s = live ? (double(xn) - c) * scale : 0.0;
     double p = !live ? 0.0 : axis ? 1.0 : double(qn);  // q s1^a, s2^b
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
       mine[a * kPowRow] = p;
       p *= s;
     }
-    const int32_t jn = j0 + 32 + src;
+    const uint32_t jn = j0 + 32 + src;
     if (jn < je) xn = co[2 * int64_t(jn)], qn = q[jn];
     __builtin_amdgcn_wave_barrier();  // the wave's LDS accesses complete in order
     for (int k = 0; k < cnt; k += 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(w1[k], w2[k], acc, 0, 0, 0);

@@ -91,3 +91,19 @@ def test_leaf_sums_at_the_end_of_the_range():
     ref = np.array([np.sum(c * w ** (k + 1)) / (k + 1) for k in range(p)])
     assert np.abs(gL[-1].cpu().numpy() - ref).max() < 1e-5 * np.abs(ref).max()
     assert abs(gb[-1].item() - c.sum()) < 1e-5 * np.abs(c).sum()
+
+
+def test_gauss_coefficients_at_the_end_of_the_range():
+    """Hermite coefficients of the last box (FP64 sums rounded once)."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    print("Gauss transform coefficients, sources end at 2^31 - 1", flush=True)
+    p, r = 3, 0.5  # box width over sqrt(2) sigma
+    sigma = float(np.float32(2.0 ** -DEPTH / (r * np.sqrt(2.0))))
+    xy, w = _last_leaf_points()
+    q = np.random.Generator(np.random.PCG64(8)).standard_normal(127).astype(np.float32)
+    A = B.fgt_hermite_coeffs(_last_rows(xy), _last_rows(q), _even_leaves(), DEPTH, p, sigma)[-1].cpu().numpy()
+    s = w * (2.0 ** -DEPTH / (np.sqrt(2.0) * sigma))
+    f = np.array([1.0, 1.0, 2.0])
+    ref = np.array([[np.sum(q * s.real ** a * s.imag ** b) / (f[a] * f[b]) for b in range(p)] for a in range(p)])
+    assert np.abs(A - ref).max() < 2.5e-7 * np.abs(ref).max()
