@@ -33,68 +33,157 @@ namespace {
 // ------------------------------------------------------- coefficients --
 
 // A[box][a][b] = 1/(a! b!) sum_j q_j s1^a s2^b, s = (x_j - s_B) / (sqrt(2) sigma),
-// FP64 sums rounded once: the (a, j) x (j, b) product of the sources' powers
+// FP64 sums rounded once, by one of two kernels.
+//
+// Boxes of many sources: the (a, j) x (j, b) product of the sources' powers
 // on FP64 matrix instructions, one wave per box.  Sources go 32 at a time:
 // each lane forms the powers of one source on one axis (P - 1 products) and
 // leaves them in the wave's LDS slice, rows kPowRow doubles apart so that the
 // 16 rows of a fragment read fall into different banks; 4 sources a k-step
 // then meet in one 16x16x4 product.  The next 32 sources load meanwhile.
-// 65536 boxes of 100 sources, p = 12: 105 us, against 224 us for a thread per
-// (box, a) that formed q s1^a anew for each source.
+//
+// Boxes of few sources: a thread per (box, a) forms q s1^a anew for each
+// source and sums it over b in registers; no lane waits for a wave's latency
+// with nothing to do.
+//
+// 65536 boxes of 100 sources, p = 12: 92 us by products, 204 by threads; 2^20
+// boxes of 0.3 sources, p = 5: 219 and 34.  Up to depth 7 products take all
+// boxes: few as they are, the two are level there (9 and 8 us at p = 5, two
+// sources a box).  Past it the mean of 64 consecutive boxes decides, at the
+// sources a box where the two meet (16 and 40 at p = 9, 8 and 16 at p = 12, 4
+// and 16 at p = 16 are either side of it for 65536 to 2^20 boxes; about 80 at p = 5);
+// a box's own count would have both kernels at work on every wave's
+// boxes near that line (61 us for 38 at p = 12, 16 sources a box).  A box of
+// four times that line is left to products whatever its neighbours have, so
+// that no thread's sum grows long.
 constexpr int kPowRow = 34;
+template <int P>
+constexpr uint32_t kMeet = 1900 / (P * P) < 128 ? 1900 / (P * P) : 128;
+constexpr int kThreadsFrom = 8;  // depth
+
+// Whether products form a box of `count` sources, `around` those of its 64.
+template <int P>
+__device__ __forceinline__ bool by_products(uint32_t count, uint32_t around) {
+  return around > 64 * kMeet<P> || count > 4 * kMeet<P>;
+}
 
 template <int P>
+__global__ __launch_bounds__(256) void fgt_coeffs_few_kernel(const float2 *__restrict__ xy, const float *__restrict__ q,
+                                                             const int32_t *__restrict__ ls, int depth, double scale,
+                                                             float *__restrict__ A) {
+  const int64_t nbox = int64_t(1) << (2 * depth);
+  const int64_t e = blockIdx.x * int64_t(256) + threadIdx.x;
+  if (e >= nbox * P) return;
+  const int64_t m = e / P;
+  const int a = int(e - m * P);
+  const int32_t jb = ls[m], je = ls[m + 1];
+  const int64_t m64 = m & ~int64_t(63);
+  if (by_products<P>(uint32_t(je - jb), uint32_t(ls[m64 + 64] - ls[m64]))) return;
+  uint32_t bx, by;
+  unmorton2(uint32_t(m), bx, by);
+  const double w = ldexp(1.0, -depth);
+  const double c1 = (double(bx) + 0.5) * w, c2 = (double(by) + 0.5) * w;
+  double acc[P];
+#pragma unroll
+  for (int b = 0; b < P; ++b) acc[b] = 0.0;
+  for (int32_t j = jb; j < je; ++j) {
+    const float2 x = xy[j];
+    const double s1 = (double(x.x) - c1) * scale, s2 = (double(x.y) - c2) * scale;
+    double p = double(q[j]);  // q s1^a, then times s2^b
+    for (int i = 0; i < a; ++i) p *= s1;
+#pragma unroll
+    for (int b = 0; b < P; ++b) {
+      acc[b] += p;
+      p *= s2;
+    }
+  }
+  double f = 1.0;  // a! b!
+  for (int i = 2; i <= a; ++i) f *= double(i);
+  float *out = A + (m * P + a) * P;
+#pragma unroll
+  for (int b = 0; b < P; ++b) {
+    if (b >= 2) f *= double(b);
+    out[b] = float(acc[b] / f);
+  }
+}
+
+// G > 1: a wave looks at G consecutive boxes and takes those that
+// fgt_coeffs_few_kernel leaves; the first sources of the next of them load
+// while a box is finished.
+template <int P, int G>
 __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restrict__ xy, const float *__restrict__ q,
                                                          const int32_t *__restrict__ ls, int depth, double scale,
                                                          float *__restrict__ A) {
   __shared__ double pow12[4][2][P * kPowRow];  // [wave][axis][power][source]
   const int64_t nbox = int64_t(1) << (2 * depth);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t m = blockIdx.x * int64_t(4) + wave;
-  if (m >= nbox) return;
-  uint32_t bx, by;
-  unmorton2(uint32_t(m), bx, by);
+  const int64_t m0 = (blockIdx.x * int64_t(4) + wave) * G;
+  if (m0 >= nbox) return;
   const double w = ldexp(1.0, -depth);
   const int axis = lane >> 5, src = lane & 31;
-  const double c = (double(axis ? by : bx) + 0.5) * w;
   double *mine = pow12[wave][axis] + src;
   typedef double d4 __attribute__((ext_vector_type(4)));
-  d4 acc = {0.0, 0.0, 0.0, 0.0};
   const int row = lane & 15, kq = lane >> 4;
   // rows and columns past P repeat row 0 and are not stored
   const double *w1 = pow12[wave][0] + (row < P ? row : 0) * kPowRow + kq;
   const double *w2 = pow12[wave][1] + (row < P ? row : 0) * kPowRow + kq;
-  const uint32_t jb = ls[m], je = ls[m + 1];  // unsigned: a step may pass 2^31
   const float *co = reinterpret_cast<const float *>(xy) + axis;
+  // lane b: the sources of box b of the wave's; unsigned: a step may pass 2^31
+  const int mybox = G == 1 ? 0 : min(lane, G - 1);
+  const uint32_t begins = ls[m0 + mybox], ends = ls[m0 + mybox + 1];
+  uint64_t left = 1;
+  if constexpr (G > 1) {
+    const int64_t m64 = m0 & ~int64_t(63);
+    left = __ballot(lane < G && by_products<P>(ends - begins, uint32_t(ls[m64 + 64] - ls[m64])));
+  }
+  if (left == 0) return;
+  int box = __ffsll(static_cast<long long>(left)) - 1;
+  uint32_t jb = __builtin_amdgcn_readlane(begins, box), je = __builtin_amdgcn_readlane(ends, box);
   float xn = 0.f, qn = 0.f;
   if (jb + src < je) xn = co[2 * int64_t(jb + src)], qn = q[jb + src];
-  for (uint32_t j0 = jb; j0 < je; j0 += 32) {
-    const int cnt = int(min(32u, je - j0));
-    const bool live = src < cnt;  // a source past the end has charge 0
-    const double s = live ? (double(xn) - c) * scale : 0.0;
-    double p = !live ? 0.0 : axis ? 1.0 : double(qn);  // q s1^a, s2^b
+  for (;;) {
+    left &= left - 1;
+    const int next = left ? __ffsll(static_cast<long long>(left)) - 1 : box;
+    const uint32_t nb = left ? __builtin_amdgcn_readlane(begins, next) : je, ne = __builtin_amdgcn_readlane(ends, next);
+    uint32_t bx, by;
+    unmorton2(uint32_t(m0) + uint32_t(box), bx, by);
+    const double c = (double(axis ? by : bx) + 0.5) * w;
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (jb == je && nb + src < ne) xn = co[2 * int64_t(nb + src)], qn = q[nb + src];  // an empty box among full ones
+    for (uint32_t j0 = jb; j0 < je; j0 += 32) {
+      const int cnt = int(min(32u, je - j0));
+      const bool live = src < cnt;  // a source past the end has charge 0
+      const double s = live ? (double(xn) - c) * scale : 0.0;
+      double p = !live ? 0.0 : axis ? 1.0 : double(qn);  // q s1^a, s2^b
 #pragma unroll
-    for (int a = 0; a < P; ++a) {
-      mine[a * kPowRow] = p;
-      p *= s;
+      for (int a = 0; a < P; ++a) {
+        mine[a * kPowRow] = p;
+        p *= s;
+      }
+      const bool last = je - j0 <= 32u;
+      const uint32_t jn = (last ? nb : j0 + 32) + src;
+      if (jn < (last ? ne : je)) xn = co[2 * int64_t(jn)], qn = q[jn];
+      __builtin_amdgcn_wave_barrier();  // the wave's LDS accesses complete in order
+      for (int k = 0; k < cnt; k += 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(w1[k], w2[k], acc, 0, 0, 0);
+      __builtin_amdgcn_wave_barrier();
     }
-    const uint32_t jn = j0 + 32 + src;
-    if (jn < je) xn = co[2 * int64_t(jn)], qn = q[jn];
-    __builtin_amdgcn_wave_barrier();  // the wave's LDS accesses complete in order
-    for (int k = 0; k < cnt; k += 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(w1[k], w2[k], acc, 0, 0, 0);
-    __builtin_amdgcn_wave_barrier();
-  }
-  if (row >= P) return;
-  double fb = 1.0;  // b!
-  for (int i = 2; i <= row; ++i) fb *= double(i);
-  float *out = A + m * (P * P) + row;
-  double fa = 1.0;  // a!
-  int done = 1;
+    if (row < P) {
+      double fb = 1.0;  // b!
+      for (int i = 2; i <= row; ++i) fb *= double(i);
+      float *out = A + (m0 + box) * (P * P) + row;
+      double fa = 1.0;  // a!
+      int done = 1;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {  // D: row a = 4 e + lane / 16, column b = lane % 16
-    const int a = 4 * e + kq;
-    for (; done < a; ++done) fa *= double(done + 1);
-    if (a < P) out[a * P] = float(acc[e] / (fa * fb));
+      for (int e = 0; e < 4; ++e) {  // D: row a = 4 e + lane / 16, column b = lane % 16
+        const int a = 4 * e + kq;
+        for (; done < a; ++done) fa *= double(done + 1);
+        if (a < P) out[a * P] = float(acc[e] / (fa * fb));
+      }
+    }
+    if (left == 0) return;
+    box = next;
+    jb = nb;
+    je = ne;
   }
 }
 
@@ -527,8 +616,18 @@ template <int P>
 void launch_coeffs_p(const float *xy, const float *q, const int32_t *ls, int depth, double scale, float *A,
                      hipStream_t s) {
   const int64_t nbox = int64_t(1) << (2 * depth);
-  hipLaunchKernelGGL(fgt_coeffs_kernel<P>, dim3(unsigned((nbox + 3) / 4)), dim3(256), 0, s,
-                     reinterpret_cast<const float2 *>(xy), q, ls, depth, scale, A);
+  const float2 *x = reinterpret_cast<const float2 *>(xy);
+#define LAUNCH(G) \
+  hipLaunchKernelGGL((fgt_coeffs_kernel<P, G>), dim3(unsigned((nbox / G + 3) / 4)), dim3(256), 0, s, x, q, ls, depth, scale, A)
+  if (depth < kThreadsFrom) {
+    LAUNCH(1);
+    return;
+  }
+  hipLaunchKernelGGL(fgt_coeffs_few_kernel<P>, dim3(blocks_of(nbox * P)), dim3(256), 0, s, x, q, ls, depth, scale, A);
+  if (depth == 8) LAUNCH(4);
+  else if (depth <= 10) LAUNCH(16);
+  else LAUNCH(64);
+#undef LAUNCH
 }
 
 template <int P>
