@@ -107,3 +107,40 @@ def test_gauss_coefficients_at_the_end_of_the_range():
     f = np.array([1.0, 1.0, 2.0])
     ref = np.array([[np.sum(q * s.real ** a * s.imag ** b) / (f[a] * f[b]) for b in range(p)] for a in range(p)])
     assert np.abs(A - ref).max() < 2.5e-7 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("rows", [N, N - 62, N - 63], ids=["all", "first past the line", "last before it"])
+def test_near_field_rows_to_the_end_of_the_range(rows):
+    """2^31 - 1 targets, and as many sources in the transpose, about three
+    columns; the last rows are checked.  The line is the number of work-items of
+    a launch."""
+    import torch
+    from paper_1009_3457_amd import _binding as B
+    print(f"near field, {rows} rows", flush=True)
+    cols = np.array([[0.9, 0.91], [0.95, 0.97], [0.99, 0.89]], np.float32)
+    cls = np.where(np.arange(65) <= 63, 0, 3).astype(np.int32)
+    rls = np.where(np.arange(65) <= 63, 0, rows).astype(np.int32)  # all in the last leaf
+    q = np.array([0.3, -0.7, 1.1], np.float32)
+    g = np.random.Generator(np.random.PCG64(9))
+    last = ((np.array([7, 7]) + g.random((100, 2))) / 8).astype(np.float32)
+    R = torch.full((rows, 2), 0.9375, device="cuda")
+    R[rows - 100:] = torch.from_numpy(last).cuda()
+    C, CL, RL = (torch.from_numpy(a).cuda() for a in (cols, cls, rls))
+    r = (last.astype(np.float64) @ [1, 1j])[:, None] - (cols.astype(np.float64) @ [1, 1j])[None, :]
+    phi = torch.zeros(rows, dtype=torch.complex64, device="cuda")
+    Q = torch.from_numpy(q).cuda()
+    B._check(B.load().fmm2d_p2p(B._p(C), B._p(Q), B._p(CL), B._p(R), B._p(RL), rows, 3, B._p(phi), None, B._stream()))
+    ref = np.log(r) @ q.astype(np.float64)
+    assert np.abs(phi[rows - 100:].cpu().numpy() - ref).max() < 1e-5 * np.abs(ref).max()
+    first = np.log(complex(0.9375, 0.9375) - cols.astype(np.float64) @ [1, 1j]) @ q.astype(np.float64)
+    assert bool((torch.view_as_real(phi[:rows - 100]).amax(dim=0) == torch.view_as_real(phi[:1])[0]).all())
+    assert bool((torch.view_as_real(phi[:rows - 100]).amin(dim=0) == torch.view_as_real(phi[:1])[0]).all())
+    assert abs(phi[0].item() - first) < 1e-5 * abs(first)
+    del phi
+    c = (g.standard_normal(3) + 1j * g.standard_normal(3)).astype(np.complex64)
+    gq, G = torch.zeros(rows, device="cuda"), torch.zeros(rows, dtype=torch.complex64, device="cuda")
+    w = torch.ones(rows, device="cuda")
+    B.p2p_backward(R, w, RL, C, CL, 3, torch.from_numpy(c).cuda(), None, gq, G)
+    gqr, Gr = (np.log(-r) @ c.astype(np.complex128)).real, (1 / r) @ c.astype(np.complex128)
+    assert np.abs(gq[rows - 100:].cpu().numpy() - gqr).max() < 1e-5 * np.abs(gqr).max()
+    assert np.abs(G[rows - 100:].cpu().numpy() - Gr).max() < 1e-5 * np.abs(Gr).max()
