@@ -517,13 +517,13 @@ def fgt_bench(name, seed, dev, steps, warmup, cpu=True, cpu_budget_s=12.0):
     ev[0].record(stream)
     A = P.fgt_hermite_coeffs(xs, qs, ls, depth, p, sigma)
     ev[1].record(stream)
-    G = P.fgt_hermite_eval(ts, depth, p, sigma, K, A)
+    G = P.fgt_hermite_eval(ts, depth, p, sigma, K, A, from_coeffs=True)
     for _ in range(warmup):
-        P.fgt_hermite_eval(ts, depth, p, sigma, K, A, G)
+        P.fgt_hermite_eval(ts, depth, p, sigma, K, A, G, from_coeffs=True)
     torch.cuda.synchronize(dev)
     ev[2].record(stream)
     for _ in range(steps):
-        P.fgt_hermite_eval(ts, depth, p, sigma, K, A, G)
+        P.fgt_hermite_eval(ts, depth, p, sigma, K, A, G, from_coeffs=True)
     ev[3].record(stream)
     torch.cuda.synchronize(dev)
     ms = ev[2].elapsed_time(ev[3]) / steps

@@ -98,6 +98,22 @@ int fgt2d_hermite_eval_place(const float *txy, int64_t nt, int depth, int p, flo
                              const float *A, const int32_t *place, float *G, void *ws,
                              size_t ws_bytes, hipStream_t stream);
 
+/*
+ * The same for an A of any origin, whose entries need not fall off with a and
+ * b as the coefficients do: the polynomial has as many terms as keep its
+ * remainder at most 2^-23 of sum |A_ab| max|h_a| max|h_b| over the
+ * neighbourhood, which is within the direct sum's own rounding; where 16 terms
+ * don't, the call is fgt2d_hermite_eval.
+ *   fgt2d_hermite_eval_any_workspace: as fgt2d_hermite_eval_workspace.
+ *   place  as in fgt2d_hermite_eval_place, or NULL: G in the targets' order.
+ * Errors: as fgt2d_hermite_eval_ws.  nt = 0 enqueues nothing.
+ */
+size_t fgt2d_hermite_eval_any_workspace(int64_t nt, int depth, int p, float sigma, int K);
+
+int fgt2d_hermite_eval_any(const float *txy, int64_t nt, int depth, int p, float sigma, int K,
+                           const float *A, const int32_t *place, float *G, void *ws,
+                           size_t ws_bytes, hipStream_t stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -65,6 +65,8 @@ _SIGNATURES = {
     # include/fgt2d.h
     "fgt2d_hermite_coeffs": (_int, [_vp, _vp, _vp, _int, _int, ctypes.c_float, _vp, _vp]),
     "fgt2d_hermite_eval": (_int, [_vp, _i64, _int, _int, ctypes.c_float, _int, _vp, _vp, _vp]),
+    "fgt2d_hermite_eval_any": (_int, [_vp, _i64, _int, _int, ctypes.c_float, _int, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "fgt2d_hermite_eval_any_workspace": (_sz, [_i64, _int, _int, ctypes.c_float, _int]),
     "fgt2d_hermite_eval_workspace": (_sz, [_i64, _int, _int, ctypes.c_float, _int]),
     "fgt2d_hermite_eval_place": (_int, [_vp, _i64, _int, _int, ctypes.c_float, _int, _vp, _vp, _vp, _vp, _sz, _vp]),
     "fgt2d_hermite_eval_ws": (_int, [_vp, _i64, _int, _int, ctypes.c_float, _int, _vp, _vp, _vp, _sz, _vp]),
@@ -562,9 +564,12 @@ def fgt_hermite_coeffs(xy_sorted, q_sorted, leaf_start, depth: int, p: int, sigm
     return A
 
 
-def fgt_hermite_eval(txy, depth: int, p: int, sigma: float, K: int, A, G=None, place=None):
+def fgt_hermite_eval(txy, depth: int, p: int, sigma: float, K: int, A, G=None, place=None, from_coeffs=False):
     """Hermite-series evaluation at the targets txy [nt, 2]: float32 [nt], the
-    value at txy[t] in G[t], or in G[place[t]] with a permutation place (int32)."""
+    value at txy[t] in G[t], or in G[place[t]] with a permutation place (int32).
+    A is any array of series; from_coeffs=True says that it is the result of
+    fgt_hermite_coeffs for the same depth, p and sigma, whose entries' decay
+    allows the boxes' series to be summed with fewer terms."""
     depth = _depth_ok(depth, lo=0)
     nt = _points(txy, "txy")
     _arg(A, "A", torch.float32, (1 << (2 * depth), p, p))
@@ -573,7 +578,9 @@ def fgt_hermite_eval(txy, depth: int, p: int, sigma: float, K: int, A, G=None, p
     dev = _dev(txy, A, G, place)
     if G is None:
         G = torch.empty(nt, dtype=torch.float32, device=dev)
-    wsb = int(load().fgt2d_hermite_eval_workspace(nt, depth, p, float(sigma), int(K)))
+    lib = load()
+    size = lib.fgt2d_hermite_eval_workspace if from_coeffs else lib.fgt2d_hermite_eval_any_workspace
+    wsb = int(size(nt, depth, p, float(sigma), int(K)))
     ws = None
     if wsb:
         try:
@@ -581,8 +588,10 @@ def fgt_hermite_eval(txy, depth: int, p: int, sigma: float, K: int, A, G=None, p
         except torch.cuda.OutOfMemoryError:  # the call without a workspace needs none
             wsb = 0
     args = (_p(txy), nt, depth, p, float(sigma), int(K), _p(A))
-    if place is None:
-        _check(load().fgt2d_hermite_eval_ws(*args, _p(G), _p(ws), wsb, _stream(dev)))
+    if not from_coeffs:
+        _check(lib.fgt2d_hermite_eval_any(*args, _p(place), _p(G), _p(ws), wsb, _stream(dev)))
+    elif place is None:
+        _check(lib.fgt2d_hermite_eval_ws(*args, _p(G), _p(ws), wsb, _stream(dev)))
     else:
-        _check(load().fgt2d_hermite_eval_place(*args, _p(place), _p(G), _p(ws), wsb, _stream(dev)))
+        _check(lib.fgt2d_hermite_eval_place(*args, _p(place), _p(G), _p(ws), wsb, _stream(dev)))
     return G

@@ -637,23 +637,30 @@ void launch_eval_p(const float *txy, int64_t nt, int depth, float inv_s, int K, 
                      reinterpret_cast<const float2 *>(txy), nt, depth, inv_s, K, A, place, G);
 }
 
-// Order of the Taylor path (0: 16 terms are not enough).
-int taylor_order(double r, int p) {
+// Order of the Taylor path (0: 16 terms are not enough).  any: for an A that
+// need not fall off as the coefficients do.  The remainder of h_a is then held
+// against Cramer's bound of h_a itself, as tau_a = sum_{m>=q} (r/2)^m/m!
+// 2^(m/2) sqrt((a+m)!/a!), largest at a = p - 1, and that of a product of two
+// is at most tau (2 + tau) of their bounds: 2^-23 at most, less than the
+// direct sum's own rounding (4e-7 to 3e-6 of the largest |G|; with the
+// coefficients' order an A of equal entries came out 7.8e-6 off for 1.0e-6
+// directly at r = 1, p = 12).
+int taylor_order(double r, int p, bool any) {
   double ta[FGT2D_MAX_P], fact = 1.0;  // (r/2)^a / a!
   for (int a = 0; a < p; ++a) {
     if (a > 0) fact *= 0.5 * r / double(a);
     ta[a] = fact;
   }
-  double rem = 0.0, best = 0.0;
+  double rem = 0.0, tau = 0.0;
   int q = 0;
   for (int m = 40; m >= 4; --m) {  // remainder of order m, smallest terms first
     double tm = 1.0, row = 0.0;
     for (int i = 1; i <= m; ++i) tm *= 0.5 * r / double(i);
     for (int a = 0; a < p; ++a) row += ta[a] * std::exp2(0.5 * (a + m)) * std::sqrt(std::tgamma(double(a + m) + 1.0));
     rem += 1.0865 * tm * row;
+    tau += tm * std::exp2(0.5 * m) * std::sqrt(std::tgamma(double(p + m)) / std::tgamma(double(p)));
     if (m > kMaxQ || (m & 1)) continue;
-    best = rem;
-    if (!(best <= 0x1p-25)) break;
+    if (!(rem <= 0x1p-25) || (any && !(tau * (2.0 + tau) <= 0x1p-23))) break;
     q = m;
   }
   return q;
@@ -666,10 +673,10 @@ int taylor_order(double r, int p) {
 // launches, (2K+1) matrix products of 16 p4 (p + q) a box (p4: p rounded up
 // to 4) and q^2 a target.  Rates measured at 65536 boxes, p = 12, K = 8:
 // 8400 us directly; 150 us of matrix products and 64 us at the targets.
-int taylor_q(int64_t nt, int depth, int p, float sigma, int K) {
+int taylor_q(int64_t nt, int depth, int p, float sigma, int K, bool any) {
   const double r = std::ldexp(1.0, -depth) / (std::sqrt(2.0) * double(sigma));
   if (!(r <= 4.0)) return 0;
-  const int q = taylor_order(r, p);
+  const int q = taylor_order(r, p, any);
   if (q == 0) return 0;
   const double w = 2.0 * K + 1.0, boxes = std::ldexp(1.0, 2 * depth), p4 = double((p + 3) / 4 * 4);
   const double wave = w * w * (double(p) * p + 4.0 * p);  // multiply-adds of one direct target
@@ -794,17 +801,25 @@ int fgt2d_hermite_eval(const float *txy, int64_t nt, int depth, int p, float sig
   return eval_direct(fn, txy, nt, depth, p, sigma, K, A, nullptr, G, stream);
 }
 
-size_t fgt2d_hermite_eval_workspace(int64_t nt, int depth, int p, float sigma, int K) {
+static size_t eval_workspace(const char *fn, int64_t nt, int depth, int p, float sigma, int K, bool any) {
   clear_error();
-  if (check_fgt_common("fgt2d_hermite_eval_workspace", depth, p, sigma) != FMM2D_OK) return 0;
+  if (check_fgt_common(fn, depth, p, sigma) != FMM2D_OK) return 0;
   if (nt <= 0 || nt >= (int64_t(1) << 31) || K < 0 || K >= (1 << depth)) return 0;
-  const int q = taylor_q(nt, depth, p, sigma, K);
+  const int q = taylor_q(nt, depth, p, sigma, K, any);
   return q ? taylor_ws(depth, p, q, K).bytes : 0;
 }
 
-static int eval_ws(const char *fn, const float *txy, int64_t nt, int depth, int p, float sigma, int K, const float *A,
-                   const int32_t *place, float *G, void *ws, size_t ws_bytes, hipStream_t stream) {
-  const int q = taylor_q(nt, depth, p, sigma, K);
+size_t fgt2d_hermite_eval_workspace(int64_t nt, int depth, int p, float sigma, int K) {
+  return eval_workspace("fgt2d_hermite_eval_workspace", nt, depth, p, sigma, K, false);
+}
+
+size_t fgt2d_hermite_eval_any_workspace(int64_t nt, int depth, int p, float sigma, int K) {
+  return eval_workspace("fgt2d_hermite_eval_any_workspace", nt, depth, p, sigma, K, true);
+}
+
+static int eval_ws(const char *fn, const float *txy, int64_t nt, int depth, int p, float sigma, int K, bool any,
+                   const float *A, const int32_t *place, float *G, void *ws, size_t ws_bytes, hipStream_t stream) {
+  const int q = taylor_q(nt, depth, p, sigma, K, any);
   if (q == 0 || ws == nullptr) return eval_direct(fn, txy, nt, depth, p, sigma, K, A, place, G, stream);
   const TaylorWs l = taylor_ws(depth, p, q, K);
   if (ws_bytes < l.bytes)
@@ -848,7 +863,7 @@ int fgt2d_hermite_eval_ws(const float *txy, int64_t nt, int depth, int p, float 
   clear_error();
   const int rc = check_eval(fn, txy, nt, depth, p, sigma, K, A, G);
   if (rc != FMM2D_OK || nt == 0) return rc;
-  return eval_ws(fn, txy, nt, depth, p, sigma, K, A, nullptr, G, ws, ws_bytes, stream);
+  return eval_ws(fn, txy, nt, depth, p, sigma, K, false, A, nullptr, G, ws, ws_bytes, stream);
 }
 
 int fgt2d_hermite_eval_place(const float *txy, int64_t nt, int depth, int p, float sigma, int K, const float *A,
@@ -859,7 +874,16 @@ int fgt2d_hermite_eval_place(const float *txy, int64_t nt, int depth, int p, flo
   if (rc != FMM2D_OK) return rc;
   if (nt == 0) return set_error(FMM2D_EINVAL, "%s: no targets", fn);
   if (!place) return set_error(FMM2D_EINVAL, "%s: place is NULL", fn);
-  return eval_ws(fn, txy, nt, depth, p, sigma, K, A, place, G, ws, ws_bytes, stream);
+  return eval_ws(fn, txy, nt, depth, p, sigma, K, false, A, place, G, ws, ws_bytes, stream);
+}
+
+int fgt2d_hermite_eval_any(const float *txy, int64_t nt, int depth, int p, float sigma, int K, const float *A,
+                           const int32_t *place, float *G, void *ws, size_t ws_bytes, hipStream_t stream) {
+  const char *fn = "fgt2d_hermite_eval_any";
+  clear_error();
+  const int rc = check_eval(fn, txy, nt, depth, p, sigma, K, A, G);
+  if (rc != FMM2D_OK || nt == 0) return rc;
+  return eval_ws(fn, txy, nt, depth, p, sigma, K, true, A, place, G, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

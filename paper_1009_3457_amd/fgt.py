@@ -22,6 +22,6 @@ def gauss_transform(xy: torch.Tensor, q: torch.Tensor, targets: torch.Tensor, de
     _, ls, flag, xs, qs = B.sort_points(xy, q, depth, want_perm=False)
     A = B.fgt_hermite_coeffs(xs, qs, ls, depth, p, sigma)
     tperm, _, tflag, ts, _ = B.sort_points(targets, None, depth)  # box order keeps each wave within a few boxes
-    G = B.fgt_hermite_eval(ts, depth, p, sigma, K, A, place=tperm)
+    G = B.fgt_hermite_eval(ts, depth, p, sigma, K, A, place=tperm, from_coeffs=True)
     B.check_domain(flag, tflag)  # waits once, after everything has been enqueued
     return G
