@@ -668,20 +668,27 @@ int taylor_order(double r, int p, bool any) {
 
 // Order q of the Taylor path for a call, 0 where the direct path is the
 // better one, by estimated microseconds.  The direct path does about
-// (2K+1)^2 (p^2 + 4p) multiply-adds a target, at least one wave's time of
-// them (few targets leave most of the chip idle).  The Taylor path has five
+// (2K+1)^2 (p^2 + 4p) multiply-adds a target, and takes at least one wave's
+// time of them, on as many boxes as the grid has.  The Taylor path has five
 // launches, (2K+1) matrix products of 16 p4 (p + q) a box (p4: p rounded up
 // to 4) and q^2 a target.  Rates measured at 65536 boxes, p = 12, K = 8:
-// 8400 us directly; 150 us of matrix products and 64 us at the targets.
+// 8400 us directly; 150 us of matrix products and 64 us at the targets.  Of
+// 1126 calls timed on both paths, 1 to 2.6e6 targets, depths 2 to 8, p 2 to 16,
+// K 1 to 16, sorted and not, those that take the Taylor path are all
+// faster by it; without the grid's limit 60 on 16 boxes were not (19 us
+// directly, 32 by the polynomial, K = 3).  The estimate of the direct path is
+// low where a wave's targets lie in many boxes: such calls (65536 targets in
+// as many boxes: 7400 us, 160) may still take it.
 int taylor_q(int64_t nt, int depth, int p, float sigma, int K, bool any) {
   const double r = std::ldexp(1.0, -depth) / (std::sqrt(2.0) * double(sigma));
   if (!(r <= 4.0)) return 0;
   const int q = taylor_order(r, p, any);
   if (q == 0) return 0;
   const double w = 2.0 * K + 1.0, boxes = std::ldexp(1.0, 2 * depth), p4 = double((p + 3) / 4 * 4);
-  const double wave = w * w * (double(p) * p + 4.0 * p);  // multiply-adds of one direct target
-  const double direct = 2.0 + std::max(wave * 4.6 / 2400.0, double(nt) * wave / 40e6);
-  const double taylor = 12.0 + boxes * w * 16.0 * p4 * (p + q) / 30e6 + double(nt) * q * q / 13e6;
+  const double side = std::ldexp(1.0, depth), reach = std::min(w, side);
+  const double box = double(p) * p + 4.0 * p;  // multiply-adds of a direct target in one box
+  const double direct = 2.0 + std::max(reach * reach * box * 4.6 / 2400.0, double(nt) * w * w * box / 40e6);
+  const double taylor = 10.4 + 0.1 * p + boxes * w * 16.0 * p4 * (p + q) / 30e6 + double(nt) * q * q / 13e6;
   return taylor < direct ? q : 0;
 }
 
