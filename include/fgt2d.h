@@ -70,10 +70,13 @@ int fgt2d_hermite_eval(const float *txy, int64_t nt, int depth, int p, float sig
 /*
  * The same with a caller workspace, which lets the neighbourhood of each box
  * be re-expanded once into a Taylor polynomial that the box's targets share:
- * far less work where a box has more than a few targets.  The polynomial's
- * remainder is at most 2^-25 per unit charge (half an ulp of the Gaussian's
- * peak) for A from fgt2d_hermite_coeffs.  FP32 arithmetic.  Targets outside
- * [0,1]^2 are evaluated as by fgt2d_hermite_eval.
+ * far less work where a box has more than a few targets.  For A from
+ * fgt2d_hermite_coeffs the polynomial's remainder is at most 2^-24 (1 + rho)
+ * per unit charge (2^-25 on each axis; rho as above; an ulp of the Gaussian's
+ * peak).  Like the cutoff's, this error is one of the charges around: where G
+ * is far smaller than they are, in the tail of a lone cluster, it has fewer
+ * digits than the direct sum's.  FP32 arithmetic.  Targets outside [0,1]^2 are
+ * evaluated as by fgt2d_hermite_eval.
  *   fgt2d_hermite_eval_workspace: bytes of device workspace for these
  *   arguments, 0 where the call would be fgt2d_hermite_eval (few targets per
  *   box, or boxes so wide against sigma that 16 terms don't reach the bound)
