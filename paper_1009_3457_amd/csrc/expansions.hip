@@ -114,10 +114,13 @@ __global__ __launch_bounds__(256) void p2m_kernel(const float2 *__restrict__ xy,
   float ar[P], ai[P];
 #pragma unroll
   for (int k = 0; k < P; ++k) ar[k] = ai[k] = 0.f;
-  const uint32_t e = ls[m + 1];  // unsigned: the step may pass 2^31
-  for (uint32_t s = uint32_t(ls[m]) + r; s < e; s += LANES) {
-    const float2 w = scaled_offset(xy[s], uint32_t(m), depth);
-    float pr = q[s], pi = 0.f;  // q w^k
+  // counted down: an index that steps past the end may pass 2^31
+  const int64_t first = ls[m] + int64_t(r);
+  xy += first;
+  q += first;
+  for (int32_t left = ls[m + 1] - ls[m] - r; left > 0; left -= LANES, xy += LANES, q += LANES) {
+    const float2 w = scaled_offset(*xy, uint32_t(m), depth);
+    float pr = *q, pi = 0.f;  // q w^k
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       ar[k] += pr;
@@ -545,18 +548,23 @@ __global__ __launch_bounds__(256) void l2p_backward_kernel(const float2 *__restr
 #pragma unroll
   for (int n = 0; n < P; ++n) ar[n] = ai[n] = 0.0;
   double sbr = 0.0, sbi = 0.0;
-  const uint32_t e = tls[m + 1];  // unsigned: the step may pass 2^31
-  for (uint32_t t = uint32_t(tls[m]) + r; t < e; t += LANES) {
-    const float2 z = txy[t];
+  const int64_t first = tls[m] + int64_t(r);
+  txy += first;
+  cphi += CPHI ? first : 0;
+  cfield += CF ? first : 0;
+  for (int32_t left = tls[m + 1] - tls[m] - r; left > 0; left -= LANES, txy += LANES) {
+    const float2 z = *txy;
     const double wr = (double(z.x) - cx) * ih, wi = (double(z.y) - cy) * ih;
     double cr = 0.0, ci = 0.0, dr = 0.0, di = 0.0;  // cphi w^n, cfield w^n / h
     if (CPHI) {
-      const float2 c = cphi[t];
+      const float2 c = *cphi;
+      cphi += LANES;
       cr = c.x, ci = c.y;
       sbr += cr, sbi += ci;
     }
     if (CF) {
-      const float2 c = cfield[t];
+      const float2 c = *cfield;
+      cfield += LANES;
       dr = double(c.x) * ih, di = double(c.y) * ih;
     }
 #pragma unroll
