@@ -54,8 +54,8 @@ namespace {
 // and 16 at p = 16 are either side of it for 65536 to 2^20 boxes; about 80 at p = 5);
 // a box's own count would have both kernels at work on every wave's
 // boxes near that line (61 us for 38 at p = 12, 16 sources a box).  A box of
-// four times that line is left to products whatever its neighbours have, so
-// that no thread's sum grows long.
+// twice that line is left to products whatever its neighbours have, as its
+// threads would be waited for (0.4 us a source).
 constexpr int kPowRow = 34;
 template <int P>
 constexpr uint32_t kMeet = 1900 / (P * P) < 128 ? 1900 / (P * P) : 128;
@@ -64,7 +64,7 @@ constexpr int kThreadsFrom = 8;  // depth
 // Whether products form a box of `count` sources, `around` those of its 64.
 template <int P>
 __device__ __forceinline__ bool by_products(uint32_t count, uint32_t around) {
-  return around > 64 * kMeet<P> || count > 4 * kMeet<P>;
+  return around > 64 * kMeet<P> || count > 2 * kMeet<P>;
 }
 
 template <int P>
@@ -86,10 +86,13 @@ __global__ __launch_bounds__(256) void fgt_coeffs_few_kernel(const float2 *__res
   double acc[P];
 #pragma unroll
   for (int b = 0; b < P; ++b) acc[b] = 0.0;
+  float2 xn = make_float2(0.f, 0.f);
+  float qn = 0.f;
+  if (jb < je) xn = xy[jb], qn = q[jb];
   for (int32_t j = jb; j < je; ++j) {
-    const float2 x = xy[j];
-    const double s1 = (double(x.x) - c1) * scale, s2 = (double(x.y) - c2) * scale;
-    double p = double(q[j]);  // q s1^a, then times s2^b
+    const double s1 = (double(xn.x) - c1) * scale, s2 = (double(xn.y) - c2) * scale;
+    double p = double(qn);  // q s1^a, then times s2^b
+    if (j + 1 < je) xn = xy[j + 1], qn = q[j + 1];
     for (int i = 0; i < a; ++i) p *= s1;
 #pragma unroll
     for (int b = 0; b < P; ++b) {
@@ -107,9 +110,10 @@ __global__ __launch_bounds__(256) void fgt_coeffs_few_kernel(const float2 *__res
   }
 }
 
-// G > 1: a wave looks at G consecutive boxes and takes those that
-// fgt_coeffs_few_kernel leaves; the first sources of the next of them load
-// while a box is finished.
+// G > 1: a wave looks at G boxes, far apart so that a cluster's go to many
+// waves (consecutive ones: 3e6 points, half of them in a 20th of each axis,
+// 640 us for 250), and takes those that fgt_coeffs_few_kernel leaves; the
+// first sources of the next of them load while a box is finished.
 template <int P, int G>
 __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restrict__ xy, const float *__restrict__ q,
                                                          const int32_t *__restrict__ ls, int depth, double scale,
@@ -117,8 +121,8 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
   __shared__ double pow12[4][2][P * kPowRow];  // [wave][axis][power][source]
   const int64_t nbox = int64_t(1) << (2 * depth);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t m0 = (blockIdx.x * int64_t(4) + wave) * G;
-  if (m0 >= nbox) return;
+  const int64_t stride = nbox / G, m0 = blockIdx.x * int64_t(4) + wave;  // box b of the wave's: m0 + b stride
+  if (m0 >= stride) return;
   const double w = ldexp(1.0, -depth);
   const int axis = lane >> 5, src = lane & 31;
   double *mine = pow12[wave][axis] + src;
@@ -129,11 +133,11 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
   const double *w2 = pow12[wave][1] + (row < P ? row : 0) * kPowRow + kq;
   const float *co = reinterpret_cast<const float *>(xy) + axis;
   // lane b: the sources of box b of the wave's; unsigned: a step may pass 2^31
-  const int mybox = G == 1 ? 0 : min(lane, G - 1);
-  const uint32_t begins = ls[m0 + mybox], ends = ls[m0 + mybox + 1];
+  const int64_t mine_at = m0 + (G == 1 ? 0 : min(lane, G - 1)) * stride;
+  const uint32_t begins = ls[mine_at], ends = ls[mine_at + 1];
   uint64_t left = 1;
   if constexpr (G > 1) {
-    const int64_t m64 = m0 & ~int64_t(63);
+    const int64_t m64 = mine_at & ~int64_t(63);
     left = __ballot(lane < G && by_products<P>(ends - begins, uint32_t(ls[m64 + 64] - ls[m64])));
   }
   if (left == 0) return;
@@ -146,7 +150,8 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
     const int next = left ? __ffsll(static_cast<long long>(left)) - 1 : box;
     const uint32_t nb = left ? __builtin_amdgcn_readlane(begins, next) : je, ne = __builtin_amdgcn_readlane(ends, next);
     uint32_t bx, by;
-    unmorton2(uint32_t(m0) + uint32_t(box), bx, by);
+    const int64_t m = m0 + box * stride;
+    unmorton2(uint32_t(m), bx, by);
     const double c = (double(axis ? by : bx) + 0.5) * w;
     d4 acc = {0.0, 0.0, 0.0, 0.0};
     if (jb == je && nb + src < ne) xn = co[2 * int64_t(nb + src)], qn = q[nb + src];  // an empty box among full ones
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(256) void fgt_coeffs_kernel(const float2 *__restric
     if (row < P) {
       double fb = 1.0;  // b!
       for (int i = 2; i <= row; ++i) fb *= double(i);
-      float *out = A + (m0 + box) * (P * P) + row;
+      float *out = A + m * (P * P) + row;
       double fa = 1.0;  // a!
       int done = 1;
 #pragma unroll

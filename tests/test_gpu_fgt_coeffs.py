@@ -1,6 +1,6 @@
 """Hermite coefficients where the choice between matrix products and a thread
 per row changes: blocks of 64 boxes at and past the line, single boxes at and
-past four times it, empty blocks, on grids whose waves take 4, 16 and 64
+past twice it, empty blocks, on grids whose waves take 4, 16 and 64
 boxes.  FP64 sums rounded once on both sides: 2^-24 relative, 2.5e-7 allowed,
 as in the other coefficient tests."""
 import numpy as np
@@ -19,11 +19,12 @@ def _counts(nbox, meet):
     blocks[0] = meet             # the mean at the line
     blocks[1] = meet
     blocks[1, 17] += 1           # and past it
-    blocks[2, 5], blocks[2, 40] = 4 * meet, 4 * meet + 1
+    blocks[2, 5], blocks[2, 40] = 2 * meet, 2 * meet + 1
     blocks[4] = g.integers(0, 3, 64)
     blocks[5] = g.integers(0, 2 * meet + 3, 64)
     blocks[7, 63] = 70 * meet + 33
     blocks[8, ::9] = 9 * meet
+    blocks[9, ::8] = 2 * meet
     blocks[-2] = g.integers(0, 2, 64)
     blocks[-1, 60:] = (1, 0, 4 * meet + 3, 2)
     return c
