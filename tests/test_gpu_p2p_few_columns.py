@@ -1,5 +1,5 @@
-"""The near field with many rows and few columns, where waves take 64 rows:
-leaves of up to 64 rows whole, larger ones in pieces, against the FP64 oracle.
+"""The near field with many rows and few columns, where waves take windows of
+64 rows: leaves of few columns in pieces of 64, others of 32, against the FP64 oracle.
 Tolerance as for the other windows: 1e-5 of the norm."""
 import numpy as np
 import pytest
@@ -12,12 +12,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,cols,depth,kind", [
-    (270000, 33750, 7, "mixed"),     # an eighth: windows of 64
-    (270000, 33751, 7, "mixed"),     # one more: of 32
-    (262144, 500, 6, "uniform"),     # 64 rows a leaf
+    (524296, 65537, 7, "mixed"),     # an eighth: windows of 64, pieces of 32 and 64
+    (524296, 65538, 7, "mixed"),     # one column more: windows of 32
+    (524288, 500, 7, "uniform"),     # 32 rows a leaf
+    (524287, 500, 6, "uniform"),     # one row less: windows of 32
+    (600003, 20, 3, "uniform"),      # leaves of thousands of rows
+    (600000, 1, 5, "mixed"),
+    (270000, 3000, 7, "mixed"),
     (262143, 500, 6, "uniform"),     # windows of 16
-    (400003, 20, 3, "uniform"),      # leaves of thousands of rows
-    (300000, 1, 5, "mixed"),
 ])
 def test_many_rows_and_few_columns_match_oracle(rows, cols, depth, kind):
     import torch
