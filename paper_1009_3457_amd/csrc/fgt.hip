@@ -655,19 +655,24 @@ void launch_eval_p(const float *txy, int64_t nt, int depth, float inv_s, int K, 
 // coefficients' order an A of equal entries came out 7.8e-6 off for 1.0e-6
 // directly at r = 1, p = 12).
 int taylor_order(double r, int p, bool any) {
-  double ta[FGT2D_MAX_P], fact = 1.0;  // (r/2)^a / a!
-  for (int a = 0; a < p; ++a) {
-    if (a > 0) fact *= 0.5 * r / double(a);
-    ta[a] = fact;
-  }
+  constexpr int kLast = 40;  // terms past it are far below the rest
+  struct Bounds {
+    double e[kLast + FGT2D_MAX_P];  // 2^(n/2) sqrt(n!)
+    Bounds() {
+      for (int n = 0; n < kLast + FGT2D_MAX_P; ++n) e[n] = std::exp2(0.5 * n) * std::sqrt(std::tgamma(double(n) + 1.0));
+    }
+  };
+  static const Bounds bounds;  // formed once: its gamma functions took 45 us of a call
+  const double *e = bounds.e;
+  double t[kLast + 1] = {1.0};  // (r/2)^m / m!
+  for (int m = 1; m <= kLast; ++m) t[m] = t[m - 1] * (0.5 * r / double(m));
   double rem = 0.0, tau = 0.0;
   int q = 0;
-  for (int m = 40; m >= 4; --m) {  // remainder of order m, smallest terms first
-    double tm = 1.0, row = 0.0;
-    for (int i = 1; i <= m; ++i) tm *= 0.5 * r / double(i);
-    for (int a = 0; a < p; ++a) row += ta[a] * std::exp2(0.5 * (a + m)) * std::sqrt(std::tgamma(double(a + m) + 1.0));
-    rem += 1.0865 * tm * row;
-    tau += tm * std::exp2(0.5 * m) * std::sqrt(std::tgamma(double(p + m)) / std::tgamma(double(p)));
+  for (int m = kLast; m >= 4; --m) {  // remainder of order m, smallest terms first
+    double row = 0.0;
+    for (int a = 0; a < p; ++a) row += t[a] * e[a + m];
+    rem += 1.0865 * t[m] * row;
+    tau += t[m] * (e[p - 1 + m] / e[p - 1]);
     if (m > kMaxQ || (m & 1)) continue;
     if (!(rem <= 0x1p-25) || (any && !(tau * (2.0 + tau) <= 0x1p-23))) break;
     q = m;
