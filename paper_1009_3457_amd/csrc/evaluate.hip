@@ -4,9 +4,9 @@
 // that only join two stages taken out.  Points and charges are sorted
 // along with the tree, L2P overwrites its sums instead of adding to cleared arrays, and
 // the near field adds them up and leaves the results in the caller's order.
-// 4096 points, depth 4: 9 launches where the stages took 28, and with one call
-// from Python where there were 14, 76 us an evaluation against 190; 2^20
-// points, depth 8, p = 12: 340 us against 457.
+// 4096 points, depth 4, p = 8: 7 launches where the stages take 17, and with
+// one call from Python where there are 11, 67 us an evaluation against 156;
+// 2^20 points, depth 8, p = 12: 302 us against 374.
 #include <algorithm>
 
 #include "fmm2d_internal.h"
@@ -179,7 +179,8 @@ int fmm2d_evaluate(const float *xy, const float *q, int64_t n, const float *txy,
     TRY(launch_sort_points(txy, nullptr, nt, depth, pl.tperm, pl.tls, pl.flags + 1, pl.ts, nullptr, w.tree, stream));
   const int64_t m = nt < 0 ? n : nt;
   TRY(launch_p2m(pl.xs, pl.qs, pl.ls, depth, p, w.M, stream));
-  TRY(launch_m2m(w.M, depth, 2, p, stream));  // M2L starts at level 2: a launch less at depths 4, 7 and 8
+  // M2L starts at level 2: ceil((depth - 2) / 3) launches for ceil(depth / 3)
+  TRY(launch_m2m(w.M, depth, 2, p, stream));
   TRY(fmm2d_m2l(w.M, w.Lm, w.bm, depth, p, 2, depth, precision, ops, ops_bytes, stream));
   TRY(launch_l2l(w.Lm, w.bm, w.L, w.b, depth, p, stream));
   TRY(launch_l2p(pl.ts, pl.tls, m, w.L, w.b, depth, p, w.phi, w.field, false, stream));

@@ -4,14 +4,16 @@
 // The sort is a least-significant-digit radix sort of the 2*depth-bit keys in
 // as few passes as digits of at most 9 bits allow (one up to depth 4, two up
 // to depth 9, three above; a 10-bit digit's runs in a tile are too short:
-// 460 us in two passes against 410 in three at 2^24 points, depth 10).  A
+// 460 us in two passes against 410 in three at 2^24 points, depth 10), or of
+// at most 8 bits below kWideFrom points (two passes up to depth 8).  A
 // pass is three launches: digit counts of each workgroup's contiguous range
-// of items, an exclusive scan of every digit's row of counts, and a scatter.  The scatter ranks a tile of items stably
+// of items, an exclusive scan of every digit's row of counts, and a scatter.
+// The scatter ranks a tile of items stably
 // (wave ballots over the digit's bits, counts per wave, a scan over the
 // digits), reorders the tile in LDS and writes runs of equal digits to
 // consecutive addresses.  Every rank follows from the input order, so the
 // result is stable and deterministic.  Up to kSmall points one workgroup
-// sorts in LDS in one launch.
+// sorts in LDS in one launch, by digits of at most 8 bits.
 //
 // Keys are formed from the points again in the first pass instead of being
 // stored by the counting launch: 8 bytes read for 4 written and 4 read.
@@ -20,7 +22,7 @@
 // read and written (53 us at the rate of a large copy), 40 + 2 x 14 us of
 // counting, 3 x 6 of scans, 26 of leaf starts.  Whole build, against 4-bit
 // digits with five launches a pass: 382 us against 762 at 2^24 points, 47
-// against 125 at 2^20 (depth 8), 13 against 48 at 4096 (depth 4).
+// against 125 at 2^20 (depth 8), 11 against 48 at 4096 (depth 4).
 #include <algorithm>
 
 #include "fmm2d_internal.h"

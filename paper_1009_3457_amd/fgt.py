@@ -23,5 +23,5 @@ def gauss_transform(xy: torch.Tensor, q: torch.Tensor, targets: torch.Tensor, de
     A = B.fgt_hermite_coeffs(xs, qs, ls, depth, p, sigma)
     tperm, _, tflag, ts, _ = B.sort_points(targets, None, depth)  # box order keeps each wave within a few boxes
     G = B.fgt_hermite_eval(ts, depth, p, sigma, K, A, place=tperm, from_coeffs=True)
-    B.check_domain(flag, tflag)  # waits once, after everything has been enqueued
+    B.check_domain(flag, tflag)  # read after everything has been enqueued
     return G

@@ -38,6 +38,19 @@ def test_series_of_any_origin_get_more_terms_or_the_direct_sum():
     assert coeffs == some > 0       # nothing to fall off
 
 
+def test_bad_arguments_are_rejected_on_host():
+    import ctypes
+    from paper_1009_3457_amd import _binding as B
+    lib, fake = B.load(), ctypes.c_void_p(0x1000)
+    nt, s = 100 * 4 ** 6, _sigma32(6, 0.5)
+    need = _sizes(nt, 6, 12, 0.5, 8)[1]
+    assert lib.fgt2d_hermite_eval_any(fake, nt, 6, 12, s, 8, fake, None, fake, fake, need - 1, None) == -5
+    assert lib.fgt2d_hermite_eval_any(fake, nt, 6, 12, s, 8, None, None, fake, fake, need, None) == -1
+    assert lib.fgt2d_hermite_eval_any(fake, nt, 6, 12, s, 8, fake, None, fake, ctypes.c_void_p(0x1008), need, None) == -1
+    assert lib.fgt2d_hermite_eval_any(fake, nt, 6, 17, s, 8, fake, None, fake, fake, need, None) == -2
+    assert lib.fgt2d_hermite_eval_any(None, 0, 6, 12, s, 8, fake, None, None, None, 0, None) == 0
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["one", "high", "random"])
 @pytest.mark.parametrize("p,K,r", [(12, 4, 1.0), (12, 5, 0.8), (12, 7, 0.6), (9, 8, 0.5), (13, 16, 0.25)])
